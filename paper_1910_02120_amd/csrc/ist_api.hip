@@ -66,7 +66,7 @@ void prof_begin(ist_ctx *ctx, int cls, hipStream_t st)
 {
     if (!ctx->prof_on) return;
     ist_ctx::ProfRec r{};
-    r.cls = cls; r.start = prof_event(ctx); r.stop = prof_event(ctx);
+    r.cls = cls; r.start = prof_event(ctx); r.stop = prof_event(ctx); r.share = 1.0; r.owner = true;
     if (!r.start || !r.stop) return;
     g_tag.kernel[0] = 0; g_tag.flops = 0.0; g_tag.bytes = 0.0;
     (void)hipEventRecord(r.start, st);
@@ -80,6 +80,20 @@ void prof_end(ist_ctx *ctx, hipStream_t st)
     (void)hipEventRecord(r.stop, st);
     snprintf(r.kernel, sizeof(r.kernel), "%s", g_tag.kernel[0] ? g_tag.kernel : kClassNames[r.cls]);
     r.flops = g_tag.flops; r.bytes = g_tag.bytes;
+}
+
+// The last record, a launch that did forward, backward-data and update products, becomes one record for each.
+void prof_split(ist_ctx *ctx, double fwd, double bwd, double upd)
+{
+    if (!ctx->prof_on || ctx->prof_recs.empty() || fwd + bwd + upd <= 0.0) return;
+    ist_ctx::ProfRec r = ctx->prof_recs.back();
+    ctx->prof_recs.pop_back();
+    const double fl[3] = {fwd, bwd, upd}, by = r.bytes;
+    const int cls[3] = {KC_GEMM_FWD, KC_GEMM_BWD_DATA, KC_GEMM_UPDATE};
+    for (int i = 0; i < 3; ++i) {
+        r.cls = cls[i]; r.flops = fl[i]; r.share = fl[i] / (fwd + bwd + upd); r.bytes = by * r.share; r.owner = i == 0;
+        ctx->prof_recs.push_back(r);
+    }
 }
 
 // launch one kernel class, bracketed by events when profiling is on
@@ -266,7 +280,8 @@ ist_status ist_create(const ist_model_desc *d, int32_t max_B, ist_ctx **out)
 ist_status ist_destroy(ist_ctx *ctx)
 {
     if (ctx) {
-        for (auto &r : ctx->prof_recs) { (void)hipEventDestroy(r.start); (void)hipEventDestroy(r.stop); }
+        for (auto &r : ctx->prof_recs)
+            if (r.owner) { (void)hipEventDestroy(r.start); (void)hipEventDestroy(r.stop); }
         for (auto e : ctx->prof_free) (void)hipEventDestroy(e);
     }
     delete ctx;
@@ -288,7 +303,8 @@ ist_status ist_profile_reset(ist_ctx *ctx)
 {
     if (!ctx) return IST_EINVAL;
     if (!ctx->prof_recs.empty()) IST_HIP(hipEventSynchronize(ctx->prof_recs.back().stop), "profile reset");
-    for (auto &r : ctx->prof_recs) { ctx->prof_free.push_back(r.start); ctx->prof_free.push_back(r.stop); }
+    for (auto &r : ctx->prof_recs)
+        if (r.owner) { ctx->prof_free.push_back(r.start); ctx->prof_free.push_back(r.stop); }
     ctx->prof_recs.clear();
     return IST_OK;
 }
@@ -303,7 +319,7 @@ ist_status ist_profile_read(ist_ctx *ctx, int32_t cls, double *total_ms, int64_t
         if (r.cls != cls) continue;
         float ms = 0.0f;
         IST_HIP(hipEventElapsedTime(&ms, r.start, r.stop), "profile read");
-        tot += ms;
+        tot += ms * r.share;
         ++n;
     }
     *total_ms = tot;
@@ -323,7 +339,7 @@ ist_status aggregate(ist_ctx *ctx, std::vector<KernelAgg> &out)
         KernelAgg *k = nullptr;
         for (auto &a : out) if (a.cls == r.cls && a.label == r.kernel) { k = &a; break; }
         if (!k) { out.push_back(KernelAgg{r.kernel, r.cls, 0.0, 0.0, 0.0, 0}); k = &out.back(); }
-        k->ms += ms; k->flops += r.flops; k->bytes += r.bytes; ++k->n;
+        k->ms += ms * r.share; k->flops += r.flops; k->bytes += r.bytes; ++k->n;
     }
     return IST_OK;
 }
@@ -1052,6 +1068,23 @@ static ist_status one_step(ist_ctx *ctx, const ist_batch *bt, float lr, int32_t 
     return IST_OK;
 }
 
+// Whether the call runs as one launch with a workgroup per subnet, and that launch's arguments.
+static bool small_network(const ist_ctx *ctx, const ist_batch *bt, float lr, int32_t k, float *loss_out, SmallArgs &a)
+{
+    if (ctx->input == IST_CSR || ctx->normalize || ctx->fused_out || ctx->t > kSmallLayers) return false;
+    a.t = ctx->t; a.G = ctx->S; a.B = bt->B; a.k = k; a.lr = lr;
+    a.x = bt->x; a.y = bt->y; a.stride_s = bt->stride_s; a.stride_k = bt->stride_k; a.loss_out = loss_out;
+    for (int l = 0; l < ctx->t; ++l) {
+        const LayerPlan &L = ctx->layer[l];
+        if (L.R > kSmallLds || L.C > kSmallLds) return false;
+        a.layer[l].W = ctx->subnets + L.off_W;
+        a.layer[l].bias = ctx->has_bias ? ctx->subnets + L.off_b : nullptr;
+        a.layer[l].R = (int32_t)L.R; a.layer[l].C = (int32_t)L.C;
+        a.layer[l].alpha = ctx->scale[l]; a.layer[l].lr = lr * ctx->scale[l];
+    }
+    return small_steps_fit(a, ctx->dtype);
+}
+
 ist_status ist_subnet_steps(ist_ctx *ctx, const ist_batch *bt, float lr, int32_t k, float *loss_out,
                             void *stream)
 {
@@ -1071,6 +1104,14 @@ ist_status ist_subnet_steps(ist_ctx *ctx, const ist_batch *bt, float lr, int32_t
     if (!(lr == lr)) return fail(ctx, IST_EINVAL, "ist_subnet_steps: lr is NaN");
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (k == 0) return IST_OK;
+    SmallArgs sa{};
+    if (small_network(ctx, bt, lr, k, loss_out, sa)) {
+        IST_RUN(KC_GEMM_UPDATE, launch_small_steps(sa, ctx->dtype, st), "local steps (small network)");
+        double w = 0.0;
+        for (int l = 0; l < ctx->t; ++l) w += 2.0 * bt->B * ctx->S * (double)k * ctx->layer[l].R * ctx->layer[l].C;
+        prof_split(ctx, w, w - 2.0 * bt->B * ctx->S * (double)k * ctx->layer[0].R * ctx->layer[0].C, w);
+        return IST_OK;
+    }
     for (int j = 0; j < k; ++j) {
         const ist_status rs = one_step(ctx, bt, lr, j, k, loss_out, st);
         if (rs != IST_OK) return rs;

@@ -100,7 +100,8 @@ struct ist_ctx {
     std::string err;
 
     // optional per-launch timing (HIP events around every launch)
-    struct ProfRec { int cls; hipEvent_t start, stop; char kernel[64]; double flops, bytes; };
+    // (a launch that does the work of several classes leaves one record for each: same events, `share` of the time)
+    struct ProfRec { int cls; hipEvent_t start, stop; char kernel[64]; double flops, bytes, share; bool owner; };
     bool prof_on = false;
     std::vector<ProfRec> prof_recs;
     std::vector<hipEvent_t> prof_free;
@@ -284,6 +285,27 @@ bool bias_jobs_all_narrow(const BiasArgs &a, int dtype);
 // `bias` (optional): narrow bias updates of the same step; *bias_done = they were done inside the shared launch
 hipError_t launch_gemm_updates(int dtype, const GemmArgs *args, int n, const BiasArgs *bias, bool *bias_done,
                                hipStream_t st);
+
+// ---- all k steps of a network whose subnets fit the LDS of a compute unit, one workgroup per subnet (ist_small.hip) ----
+constexpr int kSmallLayers = 8, kSmallLds = 160 * 1024;
+struct SmallLayer {
+    void *W, *bias;                          // packed blocks [G][R][C], [G][R] (null: no bias)
+    int32_t R, C;
+    float alpha, lr;                         // layer factor, step of the weights (lr * factor)
+    int32_t off_w, off_b, off_h, off_dz;     // LDS bytes: weights, bias, h_l, dz_l (logits first at the top layer)
+    int32_t pw, ph, pz;                      // their row pitches in bytes
+    int32_t mr, mc;                          // 2^20 over the number of 16-wide tiles of the rows / columns, rounded up
+};
+struct SmallArgs {
+    SmallLayer layer[kSmallLayers];
+    const void *x; const int32_t *y; int64_t stride_s, stride_k;
+    float *loss_out;                         // [G][k] or null
+    float lr;                                // step of the biases
+    int32_t t, G, B, k;
+    int32_t px, mx, off_x, off_y, off_loss, lds_bytes;
+};
+bool small_steps_fit(SmallArgs &a, int dtype);   // fills in the LDS layout
+hipError_t launch_small_steps(const SmallArgs &a, int dtype, hipStream_t st);
 
 // sparse-input first layer (weights stored [G][N0][w])
 struct CsrArgs {
