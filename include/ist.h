@@ -240,7 +240,8 @@ const char *ist_profile_class_name(int32_t kernel_class);
  * once, every result written once, the weights of an update read and written, the
  * ReLU mask of a backward-data product read; copy kernels: the cache-line-granular
  * minimum - rows a block touches are read whole, and rewritten whole on merge when
- * their columns are partitioned; 0 where not tracked).  All pointers [host].
+ * their columns are partitioned; 0 where not tracked).  A launch that does the work of several
+ * kernels appears as one entry for each part, with its share of the launch's time.  All pointers [host].
  */
 ist_status ist_profile_kernel_count(ist_ctx *ctx, int32_t *count);
 ist_status ist_profile_kernel(ist_ctx *ctx, int32_t index, char *label, size_t label_cap,

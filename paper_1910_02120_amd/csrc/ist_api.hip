@@ -9,11 +9,6 @@
 
 #include "ist_internal.h"
 
-namespace ist {
-hipError_t launch_perm_check(const int32_t *perm, const int32_t *invpos, int64_t N, int32_t *err,
-                             hipStream_t st);
-}
-
 using namespace ist;
 
 namespace {
@@ -82,17 +77,24 @@ void prof_end(ist_ctx *ctx, hipStream_t st)
     r.flops = g_tag.flops; r.bytes = g_tag.bytes;
 }
 
-// The last record, a launch that did forward, backward-data and update products, becomes one record for each.
-void prof_split(ist_ctx *ctx, double fwd, double bwd, double upd)
+// The last record, of a launch that did the work of several kernels, becomes one record for each part: its label (null: the
+// launch's), class, flops and bytes, and its share of the time (in proportion to `weight`).
+struct ProfPart { const char *label; int cls; double flops, bytes, weight; };
+void prof_split(ist_ctx *ctx, const ProfPart *part, int n)
 {
-    if (!ctx->prof_on || ctx->prof_recs.empty() || fwd + bwd + upd <= 0.0) return;
+    double total = 0.0;
+    for (int i = 0; i < n; ++i) total += part[i].weight;
+    if (!ctx->prof_on || ctx->prof_recs.empty() || total <= 0.0) return;
     ist_ctx::ProfRec r = ctx->prof_recs.back();
     ctx->prof_recs.pop_back();
-    const double fl[3] = {fwd, bwd, upd}, by = r.bytes;
-    const int cls[3] = {KC_GEMM_FWD, KC_GEMM_BWD_DATA, KC_GEMM_UPDATE};
-    for (int i = 0; i < 3; ++i) {
-        r.cls = cls[i]; r.flops = fl[i]; r.share = fl[i] / (fwd + bwd + upd); r.bytes = by * r.share; r.owner = i == 0;
-        ctx->prof_recs.push_back(r);
+    bool first = true;
+    for (int i = 0; i < n; ++i) {
+        if (part[i].weight <= 0.0) continue;
+        ist_ctx::ProfRec q = r;
+        if (part[i].label) snprintf(q.kernel, sizeof(q.kernel), "%s", part[i].label);
+        q.cls = part[i].cls; q.flops = part[i].flops; q.bytes = part[i].bytes; q.share = part[i].weight / total; q.owner = first;
+        ctx->prof_recs.push_back(q);
+        first = false;
     }
 }
 
@@ -460,24 +462,23 @@ static ist_status build_tables(ist_ctx *ctx, char *base, const int32_t *const *p
             IST_HIP(launch_fill_u32(ctx->workspace + ctx->hidden[l - 1].off_invpos, ctx->hidden[l - 1].N, 0xffffffffu, st),
                     "clear invpos");
     }
-    for (int l0 = 1; l0 < t; l0 += kMaxPermJobs) {   // all hidden layers (8 at a time) in two launches
+    for (int l0 = 1; l0 < t; l0 += kMaxPermJobs) {   // all hidden layers (8 at a time) in one launch
         PermJobs pj{};
         pj.S = S;
         for (int l = l0; l < t && l < l0 + kMaxPermJobs; ++l) {
             const HiddenPlan &h = ctx->hidden[l - 1];
-            pj.job[pj.njobs++] = PermJob{perm[l - 1], reinterpret_cast<int32_t *>(ctx->workspace + h.off_invpos),
-                                         reinterpret_cast<int32_t *>(base + h.off_sorted),
+            pj.job[pj.njobs++] = PermJob{perm[l - 1], reinterpret_cast<int32_t *>(base + h.off_sorted),
                                          reinterpret_cast<int32_t *>(base + h.off_slot),
                                          reinterpret_cast<int32_t *>(base + h.off_p2q),
                                          reinterpret_cast<uint32_t *>(base + h.off_mask),
-                                         reinterpret_cast<int32_t *>(base + h.off_rank), h.N};
+                                         reinterpret_cast<int32_t *>(base + h.off_rank), h.N, h.w};
         }
         IST_RUN(KC_PERM_TABLES, launch_perm_tables(pj, ctx->errflag(), st), "perm tables");
     }
     if (ctx->checked)
         for (int l = 1; l < t; ++l) {
             const HiddenPlan &h = ctx->hidden[l - 1];
-            IST_RUN(KC_PERM_TABLES, launch_perm_check(perm[l - 1], reinterpret_cast<const int32_t *>(ctx->workspace + h.off_invpos),
+            IST_RUN(KC_PERM_TABLES, launch_perm_check(perm[l - 1], reinterpret_cast<int32_t *>(ctx->workspace + h.off_invpos),
                                                       h.N, ctx->errflag(), st), "perm check");
         }
     if (ctx->checked) {
@@ -488,6 +489,64 @@ static ist_status build_tables(ist_ctx *ctx, char *base, const int32_t *const *p
     }
 
     return IST_OK;
+}
+
+// One launch for the collected jobs; the profile shows its parts under the names of the layer kinds.
+static ist_status run_row_jobs(ist_ctx *ctx, RowJobs &jobs, bool merge, bool part, hipStream_t st)
+{
+    const int m = merge && part ? 2 : (merge ? 1 : 0);
+    static const int kCls[3] = {KC_PARTITION_COPY, KC_MERGE_COPY, KC_RESAMPLE};
+    static const char *const kLabel[4][3] = {{"k_rows<gather>", "k_rows<scatter>", "k_resample_rows"},
+                                             {"k_mid<gather>", "k_mid<scatter>", "k_resample_mid"},
+                                             {"k_last<gather>", "k_last<scatter>", "k_resample_last"},
+                                             {"bias_copy", "bias_copy", "bias_copy"}};
+    if (jobs.njobs) {
+        IST_RUN(kCls[m], launch_row_jobs(jobs, merge, part, ctx->dtype, st), "block copies");
+        ProfPart parts[4];
+        for (int i = 0; i < 4; ++i)
+            parts[i] = ProfPart{kLabel[i][m], i == 3 ? KC_BIAS_COPY : kCls[m], 0.0, jobs.bytes[i], jobs.bytes[i]};
+        prof_split(ctx, parts, 4);
+    }
+    jobs.njobs = 0; jobs.blocks = 0;
+    for (double &b : jobs.bytes) b = 0.0;
+    return IST_OK;
+}
+
+// Block copies and biases of all layers: the subnets in `from` (or null) are merged into params, then those in `to` (or
+// null) are cut from it.  Large layers have launches of their own, everything else shares one.
+static ist_status copy_layers(ist_ctx *ctx, const ist_params *params, char *from, char *to, hipStream_t st)
+{
+    RowJobs jobs{};
+    jobs.G = ctx->S;
+    for (int l = 1; l <= ctx->t; ++l) {
+        const LayerPlan &L = ctx->layer[l - 1];
+        CopyArgs o{}, n{};
+        if (from) o = copy_args(ctx, from, l, params->W[l - 1]);
+        if (to) n = copy_args(ctx, to, l, params->W[l - 1]);
+        const CopyArgs *po = from ? &o : nullptr, *pn = to ? &n : nullptr;
+        // each layer adds two jobs at most: the block copy, and the biases (hidden biases travel with their neuron; the
+        // output bias is copied to every subnet and merged as the mean of the copies)
+        for (int what = 0; what < 2; ++what) {
+            if (what == 1 && !ctx->has_bias) break;
+            if (what == 0 && copy_has_own_launch(po, pn)) {
+                bool fused = false;
+                if (from && to) IST_RUN(KC_RESAMPLE, launch_resample_copy(o, n, &fused, st), "resample copy");
+                if (from && !fused) IST_RUN(KC_MERGE_COPY, launch_merge_copy(o, st), "merge copy");
+                if (to && !fused) IST_RUN(KC_PARTITION_COPY, launch_partition_copy(n, st), "partition copy");
+                continue;
+            }
+            auto add = [&]() {
+                return what == 0 ? add_row_job(jobs, po, pn)
+                                 : add_bias_job(jobs, params->b[l - 1], from ? from + L.off_b : nullptr,
+                                                to ? to + L.off_b : nullptr, po, pn);
+            };
+            if (add()) continue;
+            const ist_status rs = run_row_jobs(ctx, jobs, from != nullptr, to != nullptr, st);
+            if (rs != IST_OK) return rs;
+            if (!add()) return fail(ctx, IST_EUNSUPPORTED, "a layer of too many rows");
+        }
+    }
+    return run_row_jobs(ctx, jobs, from != nullptr, to != nullptr, st);
 }
 
 ist_status ist_partition(ist_ctx *ctx, const ist_params *params, const int32_t *const *perm,
@@ -501,24 +560,13 @@ ist_status ist_partition(ist_ctx *ctx, const ist_params *params, const int32_t *
     for (int l = 1; l < ctx->t; ++l)
         if (!perm[l - 1]) return fail(ctx, IST_EINVAL, "ist_partition: null perm");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int t = ctx->t, S = ctx->S, e = ctx->esz();
     ctx->partitioned = false;
 
     ist_status ts = build_tables(ctx, ctx->subnets, perm, st, "ist_partition");
     if (ts != IST_OK) return ts;
 
-    BiasCopyJobs bj{};
-    for (int l = 1; l <= t; ++l) {
-        const LayerPlan &L = ctx->layer[l - 1];
-        CopyArgs a = copy_args(ctx, ctx->subnets, l, params->W[l - 1]);
-        IST_RUN(KC_PARTITION_COPY, launch_partition_copy(a, st), "partition copy");
-        if (ctx->has_bias) {   // hidden biases travel with their neuron, the output bias goes to every subnet
-            if (bj.njobs == 16) { IST_RUN(KC_BIAS_COPY, launch_bias_jobs(bj, e, false, st), "partition biases"); bj.njobs = 0; }
-            if (l < t) bj.job[bj.njobs++] = BiasCopyJob{params->b[l - 1], ctx->subnets + L.off_b, a.rows, L.R * S, S, 0};
-            else bj.job[bj.njobs++] = BiasCopyJob{params->b[l - 1], ctx->subnets + L.off_b, nullptr, L.R, S, 0};
-        }
-    }
-    if (bj.njobs) IST_RUN(KC_BIAS_COPY, launch_bias_jobs(bj, e, false, st), "partition biases");
+    ts = copy_layers(ctx, params, nullptr, ctx->subnets, st);
+    if (ts != IST_OK) return ts;
     ctx->partitioned = true;
     return IST_OK;
 }
@@ -530,24 +578,7 @@ ist_status ist_merge(ist_ctx *ctx, const ist_params *params, void *stream)
     ist_status ps = check_params(ctx, params, "ist_merge");
     if (ps != IST_OK) return ps;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int t = ctx->t, S = ctx->S, e = ctx->esz();
-    BiasCopyJobs bj{};
-    for (int l = 1; l <= t; ++l) {
-        const LayerPlan &L = ctx->layer[l - 1];
-        CopyArgs a = copy_args(ctx, ctx->subnets, l, params->W[l - 1]);
-        IST_RUN(KC_MERGE_COPY, launch_merge_copy(a, st), "merge copy");
-        if (ctx->has_bias) {
-            if (l < t) {
-                if (bj.njobs == 16) { IST_RUN(KC_BIAS_COPY, launch_bias_jobs(bj, e, true, st), "merge biases"); bj.njobs = 0; }
-                bj.job[bj.njobs++] = BiasCopyJob{params->b[l - 1], ctx->subnets + L.off_b, a.rows, L.R * S, S, 0};
-            } else {
-                IST_RUN(KC_BIAS_COPY, launch_bias_mean(params->b[l - 1], ctx->subnets + L.off_b, L.R, S, ctx->dtype, st),
-                        "mean output bias");
-            }
-        }
-    }
-    if (bj.njobs) IST_RUN(KC_BIAS_COPY, launch_bias_jobs(bj, e, true, st), "merge biases");
-    return IST_OK;
+    return copy_layers(ctx, params, ctx->subnets, nullptr, st);
 }
 
 ist_status ist_bind_spare(ist_ctx *ctx, void *spare_subnets, size_t bytes)
@@ -574,34 +605,11 @@ ist_status ist_resample(ist_ctx *ctx, const ist_params *params, const int32_t *c
     for (int l = 1; l < ctx->t; ++l)
         if (!perm[l - 1]) return fail(ctx, IST_EINVAL, "ist_resample: null perm");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int t = ctx->t, S = ctx->S, e = ctx->esz();
     // tables of the new partition go to the spare buffer; a rejected perm leaves everything as it was
     ist_status ts = build_tables(ctx, ctx->spare, perm, st, "ist_resample");
     if (ts != IST_OK) return ts;
-    for (int l = 1; l <= t; ++l) {
-        const LayerPlan &L = ctx->layer[l - 1];
-        CopyArgs o = copy_args(ctx, ctx->subnets, l, params->W[l - 1]);
-        CopyArgs n = copy_args(ctx, ctx->spare, l, params->W[l - 1]);
-        bool fused = false;
-        IST_RUN(KC_RESAMPLE, launch_resample_copy(o, n, &fused, st), "resample copy");
-        if (!fused) {
-            IST_RUN(KC_MERGE_COPY, launch_merge_copy(o, st), "merge copy");
-            IST_RUN(KC_PARTITION_COPY, launch_partition_copy(n, st), "partition copy");
-        }
-        if (ctx->has_bias) {
-            if (l < t) {
-                IST_RUN(KC_BIAS_COPY, launch_bias_rows(params->b[l - 1], ctx->subnets + L.off_b, o.rows, L.R * S, e, true, st),
-                        "merge bias");
-                IST_RUN(KC_BIAS_COPY, launch_bias_rows(params->b[l - 1], ctx->spare + L.off_b, n.rows, L.R * S, e, false, st),
-                        "partition bias");
-            } else {
-                IST_RUN(KC_BIAS_COPY, launch_bias_mean(params->b[l - 1], ctx->subnets + L.off_b, L.R, S, ctx->dtype, st),
-                        "mean output bias");
-                IST_RUN(KC_BIAS_COPY, launch_bias_replicate(params->b[l - 1], ctx->spare + L.off_b, L.R, S, e, st),
-                        "replicate output bias");
-            }
-        }
-    }
+    ts = copy_layers(ctx, params, ctx->subnets, ctx->spare, st);
+    if (ts != IST_OK) return ts;
     std::swap(ctx->subnets, ctx->spare);
     return IST_OK;
 }
@@ -1109,7 +1117,11 @@ ist_status ist_subnet_steps(ist_ctx *ctx, const ist_batch *bt, float lr, int32_t
         IST_RUN(KC_GEMM_UPDATE, launch_small_steps(sa, ctx->dtype, st), "local steps (small network)");
         double w = 0.0;
         for (int l = 0; l < ctx->t; ++l) w += 2.0 * bt->B * ctx->S * (double)k * ctx->layer[l].R * ctx->layer[l].C;
-        prof_split(ctx, w, w - 2.0 * bt->B * ctx->S * (double)k * ctx->layer[0].R * ctx->layer[0].C, w);
+        const double back = w - 2.0 * bt->B * ctx->S * (double)k * ctx->layer[0].R * ctx->layer[0].C;
+        const ProfPart part[3] = {{nullptr, KC_GEMM_FWD, w, g_tag.bytes * w / (2 * w + back), w},
+                                  {nullptr, KC_GEMM_BWD_DATA, back, g_tag.bytes * back / (2 * w + back), back},
+                                  {nullptr, KC_GEMM_UPDATE, w, g_tag.bytes * w / (2 * w + back), w}};
+        prof_split(ctx, part, 3);
         return IST_OK;
     }
     for (int j = 0; j < k; ++j) {

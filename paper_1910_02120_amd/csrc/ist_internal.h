@@ -125,16 +125,18 @@ extern thread_local KernelTag g_tag;
 void tag_kernel(const char *label, double flops, double bytes);
 
 // ----------------------------------------------------------------- partition / merge
-// Block tables of several hidden layers (N neurons each, S blocks) from their permutations, two launches for
-// all of them: invpos = inverse permutation (scratch), then per block the neuron ids sorted ascending (sorted),
-// each neuron's packed position (slot), packed position by permutation position (p2q), membership bitmask per
-// block (mask) and the count of members before each 32-neuron word (rank).  Fills in the blk0 fields itself.
+// Block tables of several hidden layers (N neurons each, S blocks of w packed positions) from their permutations in one
+// launch: per block the neuron ids sorted ascending (sorted), each neuron's packed position (slot), packed position by
+// permutation position (p2q), membership bitmask per block (mask) and the count of members before each 32-neuron word
+// (rank).  *err gets bit 0 for an id outside 0 .. N - 1.
 constexpr int kMaxPermJobs = 8;
 struct PermJob {
-    const int32_t *perm; int32_t *invpos, *sorted, *slot, *p2q; uint32_t *mask; int32_t *rank; int64_t N;
+    const int32_t *perm; int32_t *sorted, *slot, *p2q; uint32_t *mask; int32_t *rank; int64_t N, w;
 };
-struct PermJobs { PermJob job[kMaxPermJobs]; int32_t inv_blk0[kMaxPermJobs + 1], sort_blk0[kMaxPermJobs + 1]; int32_t njobs, S; };
-hipError_t launch_perm_tables(PermJobs &jobs, int32_t *err, hipStream_t st);
+struct PermJobs { PermJob job[kMaxPermJobs]; int32_t njobs, S; };
+hipError_t launch_perm_tables(const PermJobs &jobs, int32_t *err, hipStream_t st);
+// bit 1 of *err if perm is not a permutation of 0 .. N - 1 (invpos: scratch, -1 everywhere on entry)
+hipError_t launch_perm_check(const int32_t *perm, int32_t *invpos, int64_t N, int32_t *err, hipStream_t st);
 
 // out[g][i][j] = W[rows ? rows[g*nr+i] : i][cols ? cols[g*nc+j] : j]  (or the
 // reverse copy when scatter is set); transposed: the subnet block is [nc][nr].
@@ -158,16 +160,23 @@ struct CopyArgs {
 hipError_t launch_partition_copy(const CopyArgs &a, hipStream_t st);
 hipError_t launch_merge_copy(const CopyArgs &a, hipStream_t st);
 hipError_t launch_resample_copy(const CopyArgs &old_part, const CopyArgs &new_part, bool *fused, hipStream_t st);
-// bias copies of several layers in one launch (partition: gather / replicate; merge: scatter of the hidden layers)
-struct BiasCopyJob { void *b; void *sub; const int32_t *rows; int64_t n; int32_t G; int32_t blk0; };
-struct BiasCopyJobs { BiasCopyJob job[16]; int32_t njobs; };
-hipError_t launch_bias_jobs(BiasCopyJobs &a, int esz, bool scatter, hipStream_t st);
-hipError_t launch_bias_rows(void *b, void *sub, const int32_t *rows, int64_t n, int esz, bool scatter,
-                            hipStream_t st);
-hipError_t launch_bias_replicate(const void *b, void *sub, int64_t n, int32_t G, int esz,
-                                 hipStream_t st);
-hipError_t launch_bias_mean(void *b, const void *sub, int64_t n, int32_t G, int dtype,
-                            hipStream_t st);
+// The layers that need no launch of their own, and all biases, of one phase (merge, partition, or one after the other)
+enum RowKind { ROW_WHOLE, ROW_MIDDLE, ROW_LAST, ROW_BIAS_HIDDEN, ROW_BIAS_OUT };
+struct RowJob {
+    void *W; int64_t ld;                                  // full matrix or bias
+    const void *sub_old; void *sub_new;                   // packed blocks merged from / cut into
+    const int32_t *rows_old, *rows_new, *slot_old, *slot_new, *cols_old, *cols_new, *rank_old, *rank_new;
+    int64_t words, nr, nc, N_out, N_in;
+    int32_t kind, vec, chunks, pad_blocks, blk0;          // workgroups blk0 .. of the launch: `chunks` for each row, then
+                                                          // pad_blocks that clear packed rows without a neuron
+};
+constexpr int kMaxRowJobs = 16;
+struct RowJobs { RowJob job[kMaxRowJobs]; int32_t njobs, G; int64_t blocks; double bytes[4] /* whole rows, middle, last, biases */; };
+bool copy_has_own_launch(const CopyArgs *old_part, const CopyArgs *new_part);
+// false: no room (launch what there is and start over)
+bool add_row_job(RowJobs &a, const CopyArgs *old_part, const CopyArgs *new_part);
+bool add_bias_job(RowJobs &a, void *b, const void *sub_old, void *sub_new, const CopyArgs *old_part, const CopyArgs *new_part);
+hipError_t launch_row_jobs(const RowJobs &a, bool merge, bool part, int dtype, hipStream_t st);
 // dst[i][j], i < nr, j < nc (the subnet's own widths, permutation order) from the packed block whose
 // rows / columns have pitch pr / pc positions; perm_r / pack_r: first permutation position and first
 // packed position of the subnet's row block (likewise for columns); null table = identity
