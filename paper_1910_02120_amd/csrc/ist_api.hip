@@ -185,7 +185,7 @@ ist_status ist_create(const ist_model_desc *d, int32_t max_B, ist_ctx **out)
     for (int l = 1; l < t; ++l) {
         HiddenPlan &h = ctx->hidden[l - 1];
         h.N = ctx->dims[l];
-        h.w = (h.N + S - 1) / S;
+        h.w = ((h.N + S - 1) / S + 7) / 8 * 8;   // whole 16-byte pieces; what is too much holds no neuron
         h.off_sorted = off; off = align_up(off + sizeof(int32_t) * h.w * S);
         h.off_slot = off;   off = align_up(off + sizeof(int32_t) * h.N);
         h.off_p2q = off;    off = align_up(off + sizeof(int32_t) * h.N);
@@ -1115,9 +1115,15 @@ ist_status ist_subnet_steps(ist_ctx *ctx, const ist_batch *bt, float lr, int32_t
     SmallArgs sa{};
     if (small_network(ctx, bt, lr, k, loss_out, sa)) {
         IST_RUN(KC_GEMM_UPDATE, launch_small_steps(sa, ctx->dtype, st), "local steps (small network)");
-        double w = 0.0;
-        for (int l = 0; l < ctx->t; ++l) w += 2.0 * bt->B * ctx->S * (double)k * ctx->layer[l].R * ctx->layer[l].C;
-        const double back = w - 2.0 * bt->B * ctx->S * (double)k * ctx->layer[0].R * ctx->layer[0].C;
+        double w = 0.0, w1 = 0.0;   // multiply-adds of the weights the subnets own, all layers and the first
+        for (int l = 1; l <= ctx->t; ++l)
+            for (int sn = 0; sn < ctx->S; ++sn) {
+                int64_t r, c;
+                own_shape(ctx, sn, l, &r, &c);
+                w += 2.0 * bt->B * (double)k * r * c;
+                if (l == 1) w1 += 2.0 * bt->B * (double)k * r * c;
+            }
+        const double back = w - w1;
         const ProfPart part[3] = {{nullptr, KC_GEMM_FWD, w, g_tag.bytes * w / (2 * w + back), w},
                                   {nullptr, KC_GEMM_BWD_DATA, back, g_tag.bytes * back / (2 * w + back), back},
                                   {nullptr, KC_GEMM_UPDATE, w, g_tag.bytes * w / (2 * w + back), w}};

@@ -62,8 +62,9 @@ struct LayerPlan {           // weight matrix l = 1..t
 
 struct HiddenPlan {          // hidden layer l = 1..t-1
     // N = q S + r neurons: the first r subnets own q + 1, the others q.  Every subnet's block is kept in
-    // w = ceil(N / S) packed positions; a position beyond the subnet's own width holds no neuron (its
-    // entry in `sorted` is -1, its weights and bias are zeros, which makes it inert in the local steps).
+    // w = ceil(N / S), rounded up to a multiple of 8, packed positions; a position beyond the subnet's own width holds
+    // no neuron (its entry in `sorted` is -1, its weights and bias are zeros, which makes it inert in the local steps).
+    // The multiple of 8 lets every product read 16-byte pieces, whatever the widths.
     int64_t N = 0, w = 0;
     int64_t width(int s, int S) const { return N / S + (s < N % S ? 1 : 0); }
     int64_t perm_start(int s, int S) const { return (int64_t)s * (N / S) + (s < N % S ? s : N % S); }

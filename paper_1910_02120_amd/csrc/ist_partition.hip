@@ -203,7 +203,8 @@ __global__ __launch_bounds__(256) void k_rows_transposed16(uint16_t *__restrict_
     uint32_t *W32 = reinterpret_cast<uint32_t *>(W);
     if (threadIdx.x < kTrQ) {
         const int64_t q = q0 + threadIdx.x;
-        start[threadIdx.x] = q < nr ? (int64_t)rows[g * nr + q] * ld + c0 : -1;
+        const int64_t r = q < nr ? rows[g * nr + q] : -1;
+        start[threadIdx.x] = r >= 0 ? r * ld + c0 : -2;     // (even: such a position's row of the tile has no misalignment)
     }
     __syncthreads();
     const int64_t ncol = nc - c0 < kTrC ? nc - c0 : kTrC;   // valid columns of this tile
@@ -251,11 +252,12 @@ __global__ __launch_bounds__(256) void k_rows_transposed16(uint16_t *__restrict_
             const int mis = (int)(e0 & 1);
             const int64_t lo = 2 * tx - mis;
             const int64_t e = e0 + lo;                      // first element of the word
-            const bool ok = e0 >= 0 && lo < ncol;           // the row count is a multiple of 8, so W holds an
-            v[pass] = W32[ok ? (e >> 1) : 0];               // even number of elements and ends on a word
+            const bool ok = e0 >= 0 && lo < ncol;           // (W holds an even number of elements: it ends on a word)
+            v[pass] = W32[ok ? (e >> 1) : 0];
         }
 #pragma unroll
-        for (int pass = 0; pass < kTrQ / 4; ++pass) tile[pass * 4 + ty][tx] = v[pass];
+        for (int pass = 0; pass < kTrQ / 4; ++pass)         // a packed position without a neuron (start < 0) is zeros
+            tile[pass * 4 + ty][tx] = start[pass * 4 + ty] >= 0 ? v[pass] : 0u;
         // the 65th word of a misaligned row
         for (int i = threadIdx.x; i < kTrQ; i += 256) {
             const int64_t e0 = start[i];
@@ -360,8 +362,9 @@ __global__ __launch_bounds__(256) void k_mid_lds(uint16_t *__restrict__ W, int64
 // Last layer (every row belongs to all subnets, columns partitioned): one workgroup
 // per row stages the row in LDS, so that the row is read/written along its memory
 // order and every packed block row is written/read as 16-byte pieces; the column
-// permutation happens inside LDS.
-template <typename E, bool SCATTER>
+// permutation happens inside LDS (a packed position without a column, -1, reads as zero and is skipped on the way back).
+// VEC: the row of the full matrix moves in 16-byte pieces as well.
+template <typename E, bool SCATTER, bool VEC>
 __global__ __launch_bounds__(256) void k_last_lds(E *__restrict__ W, int64_t ld, E *__restrict__ sub,
                                                   const int32_t *__restrict__ sorted, int64_t nr,
                                                   int64_t nc, int32_t G)
@@ -370,19 +373,26 @@ __global__ __launch_bounds__(256) void k_last_lds(E *__restrict__ W, int64_t ld,
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     E *row = reinterpret_cast<E *>(lds_raw);
     const int64_t i = blockIdx.x;
-    uint4 *full = reinterpret_cast<uint4 *>(W + i * ld);
-    const int64_t nchunk = ld / EPC;
+    E *const full = W + i * ld;
     const int64_t nunit = (int64_t)G * nc / EPC;
     if (!SCATTER) {
-        for (int64_t c = threadIdx.x; c < nchunk; c += blockDim.x)
-            reinterpret_cast<uint4 *>(row)[c] = ld_stream(full + c);
+        if (VEC) {
+            for (int64_t c = threadIdx.x; c < ld / EPC; c += blockDim.x)
+                reinterpret_cast<uint4 *>(row)[c] = ld_stream(reinterpret_cast<const uint4 *>(full) + c);
+        } else {
+            for (int64_t c = threadIdx.x; c < ld; c += blockDim.x) row[c] = full[c];
+        }
         __syncthreads();
         for (int64_t u = threadIdx.x; u < nunit; u += blockDim.x) {
             const int64_t P0 = u * EPC;
             const int64_t g = P0 / nc, q0 = P0 % nc;
             E e[EPC];
 #pragma unroll
-            for (int j = 0; j < EPC; ++j) e[j] = row[sorted[P0 + j]];
+            for (int j = 0; j < EPC; ++j) {
+                const int32_t c = sorted[P0 + j];     // (no branch around the LDS access)
+                const E v = row[c >= 0 ? c : 0];
+                e[j] = c >= 0 ? v : E(0);
+            }
             uint4 o;
             __builtin_memcpy(&o, e, 16);
             *reinterpret_cast<uint4 *>(sub + ((int64_t)g * nr + i) * nc + q0) = o;
@@ -395,11 +405,18 @@ __global__ __launch_bounds__(256) void k_last_lds(E *__restrict__ W, int64_t ld,
             E e[EPC];
             __builtin_memcpy(e, &o, 16);
 #pragma unroll
-            for (int j = 0; j < EPC; ++j) row[sorted[P0 + j]] = e[j];
+            for (int j = 0; j < EPC; ++j) {
+                const int32_t c = sorted[P0 + j];
+                row[c >= 0 ? c : ld] = e[j];          // (one spare element behind the row takes what is skipped)
+            }
         }
         __syncthreads();
-        for (int64_t c = threadIdx.x; c < nchunk; c += blockDim.x)
-            full[c] = reinterpret_cast<const uint4 *>(row)[c];
+        if (VEC) {
+            for (int64_t c = threadIdx.x; c < ld / EPC; c += blockDim.x)
+                reinterpret_cast<uint4 *>(full)[c] = reinterpret_cast<const uint4 *>(row)[c];
+        } else {
+            for (int64_t c = threadIdx.x; c < ld; c += blockDim.x) full[c] = row[c];
+        }
     }
 }
 
@@ -430,12 +447,13 @@ static bool copy_aligned(const CopyArgs &a)
 static bool copy_alone(const CopyArgs &a)
 {
     if (a.transposed) return true;
-    if (!a.cols || !copy_aligned(a)) return false;
+    if (!a.cols) return false;
     const int64_t all_rows = a.nr * a.G;
     if (a.rows)
-        return a.esz == 2 && (double)a.N_out * a.N_in * a.esz >= 64.0 * (1 << 20) && a.N_in == a.ld && a.N_in % 32 == 0 &&
+        return copy_aligned(a) && a.esz == 2 && (double)a.N_out * a.N_in * a.esz >= 64.0 * (1 << 20) && a.N_in == a.ld && a.N_in % 32 == 0 &&
                all_rows == a.N_out && a.nc * a.G == a.N_in && all_rows < 0x7fffffffLL;
-    return a.nr >= 4096 && a.nc % (16 / a.esz) == 0 && a.nc * a.G == a.N_in && a.N_in * a.esz <= 65536 && a.nr < 0x7fffffffLL;
+    return a.nr >= 4096 && reinterpret_cast<uintptr_t>(a.sub) % 16 == 0 && a.N_in == a.ld && a.N_in * a.esz < 65536 &&
+           a.nr < 0x7fffffffLL;   // (packed rows are whole 16-byte pieces)
 }
 
 template <typename E, bool SCATTER>
@@ -447,7 +465,7 @@ static hipError_t copy_typed(const CopyArgs &a, hipStream_t st)
     if (a.transposed) {
         tag_kernel(SCATTER ? "k_rows_transposed<scatter>" : "k_rows_transposed<gather>", 0.0, line_b);
         if (sizeof(E) == 2 && reinterpret_cast<uintptr_t>(W) % 4 == 0 && reinterpret_cast<uintptr_t>(sub) % 16 == 0 &&
-            a.nr % 8 == 0 && ((int64_t)a.nr * a.nc) % 8 == 0 && a.G * a.nr == a.N_out) {
+            a.nr % 8 == 0 && ((int64_t)a.nr * a.nc) % 8 == 0 && a.N_out * a.N_in % 2 == 0) {
             const int64_t ncx = (a.nc + kTrC - 1) / kTrC, nqy = (a.nr + kTrQ - 1) / kTrQ;
             const int64_t wgs = 8 * ((ncx * nqy * a.G + 7) / 8);
             if (wgs < 0x7fffffffLL) {
@@ -469,8 +487,13 @@ static hipError_t copy_typed(const CopyArgs &a, hipStream_t st)
         int th = (int)(a.N_in * a.esz / 16);
         th = th < 64 ? 64 : (th > 256 ? 256 : (th + 63) / 64 * 64);
         tag_kernel(SCATTER ? "k_last_lds<scatter>" : "k_last_lds<gather>", 0.0, line_b);
-        hipLaunchKernelGGL((k_last_lds<E, SCATTER>), dim3((unsigned)a.nr), dim3(th), (size_t)(a.N_in * sizeof(E)), st,
-                           W, a.ld, sub, a.cols, a.nr, a.nc, a.G);
+        const size_t lds = (size_t)(a.N_in * (int64_t)sizeof(E) / 16 * 16 + 16);   // the row and a spare element
+        if (copy_aligned(a))
+            hipLaunchKernelGGL((k_last_lds<E, SCATTER, true>), dim3((unsigned)a.nr), dim3(th), lds, st, W, a.ld, sub, a.cols,
+                               a.nr, a.nc, a.G);
+        else
+            hipLaunchKernelGGL((k_last_lds<E, SCATTER, false>), dim3((unsigned)a.nr), dim3(th), lds, st, W, a.ld, sub, a.cols,
+                               a.nr, a.nc, a.G);
     }
     return hipGetLastError();
 }

@@ -21,6 +21,8 @@ CASES = {   # name: (dtype, dims, S)
     "window-f32": ("f32", (3, 300001, 2), 2),
     "many-subnets-bf16": ("bf16", (6, 150, 77, 5), 70),
     "tall-last-f32": ("f32", (4, 48, 4500), 4),
+    "tall-last-uneven-bf16": ("bf16", (4, 51, 4200), 7),
+    "tall-last-uneven-aligned-f32": ("f32", (4, 52, 4200), 7),
     "large-middle-bf16": ("bf16", (8, 8192, 4096, 4), 4),
     "many-layers-f32": ("f32", (9,) + (24, 17) * 5 + (3,), 3),
 }
