@@ -948,6 +948,100 @@ __global__ __launch_bounds__(256) void k_splitk_finish(GemmArgs a, const float *
     epi8<D, EPI>(a, g, g, m, n0, val, vecC, bias8);
 }
 
+// ---------------------------------------------------------------- forward product of a few samples
+//   C_g[m][n] = act(alpha sum_k A_g[m][k] W_g[n][k] + bias_g[n]),  m < 16 TM (TM = 1, 2)
+// Bound by the one read of W: a workgroup owns 16 rows of W over the whole of k, so a layer of 4096 neurons already has
+// a workgroup for every CU without splitting k into partial products and a second launch.  Its 8 waves share k by
+// stages of 4 x 64 bytes of a row; W and A go from memory straight into MFMA operand registers (16 bytes of a row per
+// lane, the order of k is the same for both operands), the next stage requested before the current one is multiplied:
+// 64 KB of W in flight per workgroup, no barrier until the waves' sums meet in LDS, in fixed order.  (64 x 32 and 64 x 64
+// tiles filled an eighth of the chip or paid for partial products: 1024-4096-4096-35, 8 samples, f32: 85 us for the pass, of
+// which W's 84 MB need 17 us; now 41 us.  bf16: 55 -> 25 us.)
+template <typename D> struct Mma16;
+template <> struct Mma16<F32> {
+    __device__ static inline f32x4 mma(uint4 a, uint4 b, f32x4 c)
+    {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+    }
+};
+template <> struct Mma16<BF16> {
+    __device__ static inline f32x4 mma(uint4 a, uint4 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+
+template <typename D, int EPI, int TM>
+__global__ __launch_bounds__(512, 2) void k_gemm_few_rows(GemmArgs a, int tiles)
+{
+    using T = typename D::T;
+    constexpr int WAVES = 8, U = 4;
+    constexpr int CH = 16 / D::kBytes;       // k values of a 16-byte piece
+    constexpr int KU = 4 * CH, KS = U * KU;  // k values per load of a wave (64 bytes of 16 rows), per stage
+    __shared__ float red[WAVES][TM][64][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15;
+    const int g = blockIdx.x / tiles, n0 = (blockIdx.x - g * tiles) * 16;
+    const T *Z = static_cast<const T *>(a.zeros);
+    const T *W = n0 + r16 < a.N ? static_cast<const T *>(a.B) + (int64_t)g * a.gB + (int64_t)(n0 + r16) * a.sbn : nullptr;
+    const T *A[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+        A[i] = 16 * i + r16 < a.M ? static_cast<const T *>(a.A) + (int64_t)g * a.gA + (int64_t)(16 * i + r16) * a.sam : nullptr;
+    struct Stage { uint4 w[U], h[TM][U]; };
+    auto load = [&](Stage &s, int it) {      // a piece outside the operand comes from the block of zeros
+        const int k0 = (it * WAVES + wave) * KS + (lane >> 4) * CH;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * KU;
+            s.w[u] = *reinterpret_cast<const uint4 *>(W && k < a.K ? W + k : Z);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) s.h[i][u] = *reinterpret_cast<const uint4 *>(A[i] && k < a.K ? A[i] + k : Z);
+        }
+    };
+    f32x4 acc[TM][U];   // a sum per load of a stage: chains of K / 32 terms, four independent MFMAs in a row
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[i][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto multiply = [&](const Stage &s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[i][u] = Mma16<D>::mma(s.w[u], s.h[i][u], acc[i][u]);
+    };
+    const int nit = (a.K + WAVES * KS - 1) / (WAVES * KS);
+    Stage s0, s1;
+    load(s0, 0);
+    for (int it = 0; it < nit; it += 2) {    // stages past the end of k are zeros
+        load(s1, it + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(s0);
+        load(s0, it + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(s1);
+    }
+    // a lane holds sample 16 i + lane % 16, neurons n0 + 4 (lane / 16) .. + 3
+#pragma unroll
+    for (int i = 0; i < TM; ++i) *reinterpret_cast<f32x4 *>(red[wave][i][lane]) = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+    __syncthreads();
+    for (int o = threadIdx.x; o < TM * 256; o += 64 * WAVES) {
+        const int i = o >> 8, mi = (o >> 4) & 15, ni = o & 15;
+        const int m = 16 * i + mi, n = n0 + ni;
+        if (m >= a.M || n >= a.N) continue;
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) v += red[w][i][(ni >> 2) * 16 + mi][ni & 3];
+        const float b = a.bias ? D::ld(static_cast<const T *>(a.bias) + (int64_t)g * a.gBias + n) : 0.0f;
+        v = fmaf(a.alpha, v, b);
+        const int64_t ci = (int64_t)g * a.gC + (int64_t)m * a.ldc + n;
+        if (EPI == EPI_FWD_RELU) static_cast<T *>(a.C)[ci] = D::cvt(v > 0.0f ? v : 0.0f);
+        else static_cast<float *>(a.C)[ci] = v;
+    }
+}
+
 // 16-byte loads need an aligned base and group stride and a pitch that is a multiple
 // of the chunk size.  The contiguous extent may end inside a chunk when the pitch is
 // padded: along m/n the extra elements only feed output rows/columns that the epilogue
@@ -1114,6 +1208,19 @@ int gemm_splits(int dtype, int epi, const GemmArgs &a)
     return plan_for(a, epi, dtype == IST_BF16 ? 2 : 4).splits;
 }
 
+// Forward products of a few samples whose rows of W are long enough for a stage of every wave (2 KB).  Every workgroup
+// reads all of A, which is as much as its rows of W at 16 samples and twice that at 32: up to 16 samples it is faster at all
+// sizes measured (rows up to 32 KB, up to 8192 neurons), above that only while every CU has at most one workgroup and the
+// rows are at most 16 KB: with longer ones a narrow layer, of which one or a few workgroups read everything, is better
+// off with k split over the chip.  f32, 16 / 32 samples, before -> now: 1024-4096-4096-35: 87 -> 47 / 91 -> 62 us;
+// 2048-8192-8192-200: 175 -> 131 us / 177 us, and 199 us with this kernel for its last layer (187 us for all layers).
+static bool few_rows(const GemmArgs &a, int esz)
+{
+    const int64_t wgs = (int64_t)((a.N + 15) / 16) * a.G, row = (int64_t)a.K * esz;
+    return (a.M <= 16 ? wgs <= 512 && row <= 32768 : a.M <= 32 && wgs <= 256 && row <= 16384) && row >= 2048 &&
+           !a.keep_partial && a.K % (16 / esz) == 0;
+}
+
 template <typename D, bool AK, bool BKC, int EPI, bool VEC>
 static hipError_t launch_vec(const GemmArgs &a, hipStream_t st)
 {
@@ -1124,6 +1231,18 @@ static hipError_t launch_vec(const GemmArgs &a, hipStream_t st)
     snprintf(lab, sizeof(lab), "%s_%s%s", kEpi[EPI], esz == 2 ? "bf16" : "f32", VEC ? "" : "_novec");
     s_label = lab;
     s_bytes = algo_bytes(a, EPI, esz);
+    if constexpr (VEC && AK && BKC && (EPI == EPI_FWD_RELU || EPI == EPI_FWD_LOGITS)) {
+        if (few_rows(a, esz)) {
+            const int tiles = (a.N + 15) / 16;
+            char label[64];
+            snprintf(label, sizeof(label), "gemm_%s_few_rows_x%d", lab, a.M <= 16 ? 16 : 32);
+            tag_kernel(label, 2.0 * a.M * a.N * (double)a.K * a.G, s_bytes);
+            const dim3 grid((unsigned)((int64_t)tiles * a.G));
+            if (a.M <= 16) hipLaunchKernelGGL((k_gemm_few_rows<D, EPI, 1>), grid, dim3(512), 0, st, a, tiles);
+            else hipLaunchKernelGGL((k_gemm_few_rows<D, EPI, 2>), grid, dim3(512), 0, st, a, tiles);
+            return hipGetLastError();
+        }
+    }
     const SplitPlan p = plan_for(a, EPI, esz);
     if (p.tile == 128) {
         constexpr int KTB = Cfg<D>::KT_BIG, STB = Cfg<D>::ST_BIG;

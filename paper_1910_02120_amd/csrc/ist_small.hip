@@ -28,7 +28,6 @@ namespace small {
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
 constexpr int kXRegs = 8;   // 64-value pieces of the next mini-batch a wave holds in registers
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // k-step unit: fragments of 16 rows (or columns) and U values of k
 template <typename D> struct Unit;
